@@ -364,7 +364,10 @@ hom_status hom_gani_matrices(hom_problem* pb, const double* const* primal, const
  * row forward pass.  The slot's scratch vectors are overwritten. */
 hom_status hom_profile_passes(hom_problem* pb, int32_t dual, int32_t nload, int32_t reps, double* ms_out);
 
-/* Release the handle (host memory only; the workspace stays with the caller). */
+/* Release the handle (host memory only; the workspace stays with the caller).
+ * Waits for the work on the problem's stream first, so that the workspace and
+ * the Fourier data may be freed when this returns, also if the problem never
+ * solved; the stream must exist until then. */
 void hom_destroy(hom_problem* pb);
 
 /* ---- Batched solves.  A batch groups n problems with identical hom_desc and

@@ -3413,6 +3413,9 @@ void hom_batch_destroy(hom_batch* b) {
 
 void hom_destroy(hom_problem* pb) {
   if (!pb) return;
+  // the set-up and other calls that do not wait may still be writing the workspace, which the caller
+  // frees after this (an idle stream costs about a microsecond)
+  (void)hipStreamSynchronize(pb->stream);
   hom_batch_destroy(pb->pair);
   for (int k = 0; k < 2; ++k)
     for (int l = 0; l <= kMaxLoads; ++l) {
