@@ -1242,9 +1242,24 @@ bool reg_split(int M, int* A, int* B) {
 // Splits and tile shapes of the register passes for the lengths of g.  A block
 // has 256 threads, one A- or B-point DFT each: as many lines as fill them,
 // within an LDS budget that leaves several blocks per CU.
+//
+// 125 = 25 * 5 is the one split whose larger factor is of class 27 and whose
+// other one is below 9: its 25-point step has 5 threads per line, 40 of a FP64
+// column block's 256.  In 3D FP64 the generic passes (three radix-5 passes) are
+// the faster ones on that axis once the chip is full (8 cells of 125^3, three
+// loads: first 288 us in registers against 169, column 1831 against 836,
+// with all components 3468 against 937, last 233 against 143); the middle pass
+// is not (349 against 427), nor are the 2D passes (one cell of 125^2: column 24
+// against 46), FP32, a column pass of one round of blocks (two of 80 KB per CU;
+// one cell on 125 x 25 x 25: 25 against 37) or rows of fewer pairs than the chip
+// has CUs (one cell on 25 x 25 x 125: a solve's iteration 65 against 69).
 void set_reg_passes(Geo& g, size_t cs) {
   for (int a = 0; a < 3; ++a) reg_split(g.M[a], &g.rA[a], &g.rB[a]);
   auto T = [&](int a) { return g.rA[a] > g.rB[a] ? g.rA[a] : g.rB[a]; };
+  auto narrow = [&](int a) {
+    return g.d == 3 && cs == sizeof(Cx<double>) && T(a) > 16 && (g.rA[a] < g.rB[a] ? g.rA[a] : g.rB[a]) < 9;
+  };
+  if (narrow(2) && g.Q > 256) g.rA[2] = g.rB[2] = 0;
   if (g.rA[2]) {
     const int P = g.d == 2 ? 1 : g.P;
     int G = kBlock / (2 * P * T(2));
@@ -1259,6 +1274,8 @@ void set_reg_passes(Geo& g, size_t cs) {
     const int nl = T(0) <= 9 ? 28 : (T(0) <= 16 ? 16 : (cs == sizeof(Cx<float>) ? 16 : 8));
     g.rgT = nl / g.P;
     if (g.rgT < 1 || (size_t)g.M[0] * nl * cs > kLdsMax) g.rA[0] = g.rB[0] = 0;
+    const long npts = (long)g.M[1] * g.M[2];
+    if (narrow(0) && (g.nc > 1 ? npts / g.rgT : npts * g.P / nl) > 512) g.rA[0] = g.rB[0] = 0;
   }
   if (g.rA[1]) {
     int nl = kBlock / T(1);
