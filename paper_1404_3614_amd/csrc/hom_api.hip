@@ -475,12 +475,21 @@ size_t carve(const hom_desc* desc, int max_loads, const Sizes& z, hom_problem* p
   return off;
 }
 
-// The FP64 quadrature of the bounds in 2D with a factor above 16 runs in the generic column pass: a register
-// block holds 8 lines there, 4 points of 2 packs, so its rows are 64-byte runs (32 cells on 625^2, the other side
-// iterating beside it: 409 us against 296); with smaller factors (16 and 28 lines) and in 3D the register pass is
-// the faster one (32 cells of 41^3: 523 against 1072).
+// The FP64 quadrature of the bounds (every pack of a point in one block) keeps the generic column pass
+//   - in 3D where a block of the register pass holds fewer grid points than threads (M0 < 256 / points) and there
+//     are more blocks than CUs.  Bounds of 8 cells: 75^3 735 us against 894 in registers, 9 x 625 x 9 222 against
+//     395, 25 x 25 x 225 241 against 350; with more points per block the register pass is the faster one (81^3 599
+//     against 884, 135^3 3593 against 4488), with fewer blocks about even (one cell of 27^3: 129 against 137);
+//   - in 2D for 125 = 25 * 5, with generic rows beside it (64 cells of 125^2: a solve 5.22 ms against 5.24).
+// Other 2D lengths: 16 cells of 405^2 275 against 336, of 625^2 467 against 513, of 729^2 851 against 899.
 void quad_passes(Geo& g) {
-  if (g.d == 2 && std::max(g.rA[0], g.rB[0]) > 16) g.rA[0] = g.rB[0] = 0;
+  if (!g.rA[0]) return;
+  if (g.d == 3) {
+    const long blocks = ((long)g.M[1] * g.M[2] + g.rgT - 1) / g.rgT;
+    if (g.M[0] * g.rgT < 256 && blocks > 256) g.rA[0] = g.rB[0] = 0;
+  } else if (std::max(g.rA[0], g.rB[0]) > 16 && std::min(g.rA[0], g.rB[0]) < 9) {
+    g.rA[0] = g.rB[0] = g.rA[2] = g.rB[2] = 0;
+  }
 }
 
 // P_override: the packs of a bound evaluation.

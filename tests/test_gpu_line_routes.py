@@ -56,3 +56,18 @@ def test_operator_route(N, M, same, full, dual, monkeypatch):
     x = _fields(pb, dual)[0]
     a, b = _both(monkeypatch, lambda: pb.apply(x, dual).cpu().numpy())
     _check(a, b, same)
+
+
+# the quadrature of the bounds: registers in 2D but for 25 * 5 (generic rows with it), in 3D where a block of the
+# register pass has a grid point per thread
+@pytest.mark.parametrize("dual", [False, True])
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("N,M,same", [
+    ((23, 13), (625, 1125), False), ((187, 13), (375, 1125), False), ((13, 13), (25, 1125), False),
+    ((63, 13), (125, 1125), True), ((63, 41), (125, 81), True), ((41, 63), (81, 125), False),
+    ((5, 187, 3), (9, 1125, 125), True), ((23, 23, 3), (75, 1125, 125), True), ((23, 23, 3), (81, 1125, 125), False)])
+def test_quadrature_route(N, M, same, full, dual, monkeypatch):
+    pb = _problem(N, M, full)
+    x = _fields(pb, dual)
+    a, b = _both(monkeypatch, lambda: pb.bounds(None, x)["B_up"] if dual else pb.bounds(x, None)["A_up"])
+    _check(a, b, same)
