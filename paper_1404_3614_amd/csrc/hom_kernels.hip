@@ -1065,25 +1065,28 @@ static_assert(sizeof(InclArg) <= 3840 && sizeof(InclPairArg) <= 3840, "kernel ar
 // A_hat(n) = A0 delta_n0 + sum_j A_j f_hat_j(n) exp(-2 pi i sum n_a x_a / Y_a) on Z_M
 // (eq. A_with_inclusions, Remark inclusion; ball: textbook transform of a ball),
 // for NS = 1 series or for A and A^-1 together (their box and ball factors are
-// the same).  A block takes R rows (j0, j1) and a run of up to kBlock points of
-// the last axis; the factors of the first two axes (box sides and phase) are
+// the same).  A block takes kBlock points of up to R rows (j0, j1), from point
+// blockIdx.x * span; the factors of the first two axes (box sides and phase) are
 // the row's, computed once per row into LDS, so a point evaluates one sine and
 // one phase per inclusion instead of three sines and the whole phase.  Bound by
-// those FP64 sines.  Measured, both series: 10 boxes on 125^2 2 x 9.1 -> 7.9 us,
-// 10 balls on 81^3 (their factor has no split over the axes) 2 x 84 -> 86 us.
+// those FP64 sines, so above 600 blocks (two per CU) the blocks run across rows
+// and no lane idles: 100 balls, both series, on 135^3 2.8 ms against 5.2 with
+// whole rows, on 75^3 0.59 against 0.66, 400 boxes on 405^2 0.86 against 1.01.
+// Smaller grids wait for one chain of sines and take whole rows (400 boxes on
+// 135^2 0.46 ms against 0.52, on 375^2 0.82 against 0.86).  Before the row
+// factors, both series: 10 boxes on 125^2 2 x 9.1 -> 7.9 us, 10 balls on 81^3
+// (their factor has no split over the axes) 2 x 84 -> 86 us.
 constexpr int kInclChunk = 32;   // inclusions whose row factors are in LDS at a time
 template <int NC, int NS, typename T>
 __global__ __launch_bounds__(kBlock) void k_coef_incl(int M0, int M1, int M2, double iY0, double iY1, double iY2, T tab,
-                                                      int n_incl, int R, Cx<double>* __restrict__ out0,
-                                                      Cx<double>* __restrict__ out1) {
+                                                      int n_incl, int span, int R,
+                                                      Cx<double>* __restrict__ out0, Cx<double>* __restrict__ out1) {
   extern __shared__ __align__(16) unsigned char smem[];
   Cx<double>* rowf = reinterpret_cast<Cx<double>*>(smem);   // [R][kInclChunk]
-  const size_t Mt = (size_t)M0 * M1 * M2;
-  const int rows = M0 * M1, row0 = blockIdx.x * R;
-  // one thread per point: with R > 1 the rows are whole (M2 points each)
-  const int lr = R > 1 ? (int)threadIdx.x / M2 : 0;
-  const int j2 = R > 1 ? (int)threadIdx.x - lr * M2 : (int)(blockIdx.y * kBlock + threadIdx.x);
-  const bool ok = lr < R && row0 + lr < rows && j2 < M2;
+  const size_t Mt = (size_t)M0 * M1 * M2, t0 = (size_t)blockIdx.x * span + blockIdx.y * kBlock;
+  const int rows = M0 * M1, row0 = (int)(t0 / M2);
+  const int off = (int)(t0 - (size_t)row0 * M2) + (int)threadIdx.x, lr = off / M2, j2 = off - lr * M2;
+  const bool ok = lr < R && row0 + lr < rows;
   const int row = ok ? row0 + lr : row0;
   const int n0 = fr(row / M1, M0), n1 = fr(row % M1, M1), n2 = fr(ok ? j2 : 0, M2);
   double re[NS][NC], im[NS][NC];
@@ -1628,14 +1631,18 @@ hipError_t launch_extract_half(const Geo& g, const CoefJob* jobs, const CoefJob&
 template <int NS, typename T>
 static hipError_t run_coef_incl(const int* Mint, const double* iY, int nc, const T& tab, int n_incl, Cx<double>* out0,
                                 Cx<double>* out1, hipStream_t st) {
-  const long rows = (long)Mint[0] * Mint[1];
-  const int R = Mint[2] <= kBlock / 2 ? kBlock / Mint[2] : 1;
-  const dim3 grid((unsigned)((rows + R - 1) / R), R > 1 ? 1 : (Mint[2] + kBlock - 1) / kBlock);
+  const size_t rows = (size_t)Mint[0] * Mint[1], points = rows * Mint[2];
+  const bool whole = points <= 600 * kBlock;
+  const int R = !whole ? (kBlock + Mint[2] - 2) / Mint[2] + 1 : std::max(kBlock / Mint[2], 1);
+  const int span = whole ? R * Mint[2] : kBlock;
+  const size_t blocks = (points + span - 1) / span;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks, whole ? (span + kBlock - 1) / kBlock : 1);
   const size_t lds = (size_t)R * kInclChunk * sizeof(Cx<double>);
 #define HOM_IN(NC)                                                                                                   \
   if (nc == NC) {                                                                                                   \
     hipLaunchKernelGGL((k_coef_incl<NC, NS, T>), grid, dim3(kBlock), lds, st, Mint[0], Mint[1], Mint[2], iY[0], iY[1], \
-                       iY[2], tab, n_incl, R, out0, out1);                                                          \
+                       iY[2], tab, n_incl, span, R, out0, out1);                                                    \
     return hipGetLastError();                                                                                       \
   }
   HOM_IN(1) HOM_IN(3) HOM_IN(6)

@@ -48,3 +48,23 @@ def test_inclusion_coefficients(d, N, iso, balls, n):
         for got in (pair, one):
             for c, (i, j) in enumerate(comp):
                 assert np.abs(got[c].cpu().numpy() - ref[i, j]).max() <= tol, (inverse, c)
+
+
+# above 600 blocks the blocks run across rows, from 5 points to longer than a block; below, whole rows per block
+@pytest.mark.parametrize("N,M", [((3, 3), (405, 405)), ((3, 3), (729, 225)), ((3, 3, 3), (225, 225, 5)),
+                                 ((3, 3, 3), (25, 81, 81)), ((3, 3, 3), (27, 45, 135)), ((3, 3), (375, 375)),
+                                 ((3, 3, 3), (5, 9, 135)), ((3, 3), (5, 5))])
+@pytest.mark.parametrize("iso,n", [(True, 5), (False, 40)])
+def test_blocks_across_rows(N, M, iso, n):
+    import paper_1404_3614_amd as H
+    d = len(N)
+    cell = _cell(d, n, iso, d == 3, seed=n + d)
+    got = H.coef_from_cell(cell, N, M=M)
+    comp = [(0, 0)] if iso else ([(0, 0), (1, 1), (0, 1)] if d == 2 else
+                                 [(0, 0), (1, 1), (2, 2), (0, 1), (0, 2), (1, 2)])
+    for inverse in (False, True):
+        ref = co.fourier_coefficients(cell, M, inverse=inverse)
+        f = np.linalg.inv if inverse else np.asarray
+        tol = 1e-14 * (np.abs(f(cell.A0)).max() + sum(np.abs(f(A) - f(cell.A0)).max() for A in cell.A))
+        for c, (i, j) in enumerate(comp):
+            assert np.abs(got[int(inverse)][c].cpu().numpy() - ref[i, j]).max() <= tol, (inverse, c)
