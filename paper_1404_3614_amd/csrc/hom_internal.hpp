@@ -242,12 +242,11 @@ struct CoefJob {
   float* p[2];             // FP32 grid values in plane order, or null
 };
 // Register passes of any length (hom_line.hpp); false when the geometry has no split for the axis.
-// split: the rows go through HBM (long-row form).
 bool reg_split(int M, int* A, int* B);
 void set_reg_passes(Geo& g, size_t csize);
 namespace ln {
 template <typename R>
-bool reg_row(bool first, bool split, const Geo& g, const UnitDev* units, int n, int mode, int jstep, const int* iter_base,
+bool reg_row(bool first, const Geo& g, const UnitDev* units, int n, int mode, int jstep, const int* iter_base,
              hipStream_t st, hipError_t* err);
 template <typename R>
 bool reg_mid(const Geo& g, const UnitDev* units, int n, int flags, hipStream_t st, hipError_t* err);

@@ -1287,14 +1287,14 @@ void set_reg_passes(Geo& g, size_t cs) {
   }
 }
 
-// The fused row passes hold both lines of a row pair (2P complex lines of M2)
-// in LDS; beyond the LDS size or the butterfly registers they run as a gather
-// (or epilogue) kernel plus a separate row transform over HBM.
-static bool force_split() { return std::getenv("HOM_LONG_ROWS") != nullptr; }  // the split form at any size (tests)
-
+// The generic fused row passes hold both lines of a row pair (2P complex lines
+// of M2) in LDS; beyond the LDS size or the butterfly registers they run as a
+// gather (or epilogue) kernel plus a separate row transform over HBM.
+// HOM_LONG_ROWS selects that form wherever the generic row passes run, at any
+// size (tests; with HOM_NO_FAST for lengths that have register passes).
 template <typename R>
 static bool rows_fit(const Geo& g, size_t extra) {
-  if (force_split()) return false;
+  if (std::getenv("HOM_LONG_ROWS")) return false;
   const int nl = 2 * g.P;
   const size_t lds = extra + (size_t)g.M[2] * nl * sizeof(Cx<R>);
   return lds <= kLdsMax && (max_butterflies(g.pl[2], g.M[2], nl) + kBlock - 1) / kBlock <= 16;
@@ -1342,7 +1342,7 @@ hipError_t launch_first(const Geo& g, const UnitDev* units, int nunits, int mode
   }
   {
     hipError_t e;
-    if (ln::reg_row<R>(true, force_split(), g, units, nunits, mode, jstep, iter_base, st, &e)) return e;
+    if (ln::reg_row<R>(true, g, units, nunits, mode, jstep, iter_base, st, &e)) return e;
   }
   const int nl = 2 * g.P;
   const size_t staged = align16((size_t)g.L * g.m * g.N[2] * sizeof(Cx<double>));
@@ -1361,7 +1361,7 @@ hipError_t launch_last(const Geo& g, const UnitDev* units, int nunits, int mode,
   }
   {
     hipError_t e;
-    if (ln::reg_row<R>(false, force_split(), g, units, nunits, mode, jstep, iter_base, st, &e)) return e;
+    if (ln::reg_row<R>(false, g, units, nunits, mode, jstep, iter_base, st, &e)) return e;
   }
   const int nl = 2 * g.P;
   if (!rows_fit<R>(g, 0)) return launch_last_long<R>(g, units, nunits, mode, jstep, iter_base, st);

@@ -331,8 +331,8 @@ __global__ __launch_bounds__((ColShape<R, RM>::NT)) void k_col_reg(Geo g, const 
 
 // ============================================================== lines along an axis
 // Transforms of strided lines without pointwise work: the middle axis of 3D
-// passes (zero-padded or truncated), the coefficient set-up, and the rows of
-// the split row passes.  Element e of block x is line x nl + l; index i of the
+// passes (zero-padded or truncated), the coefficient set-up, images and GaNi
+// coefficients.  Element e of block x is line x nl + l; index i of the
 // line is at (i * stride + line offset).  With contiguous lines (stride 1) the
 // thread index runs along the line instead of across the lines, so that global
 // accesses stay contiguous.
@@ -443,14 +443,6 @@ __global__ __launch_bounds__(kBlock) void k_mid_reg(Geo g, const UnitDev* __rest
   line_body<R, RM>(a, in, out, reinterpret_cast<const Cx<R>*>(g.tw[1]), inverse, reinterpret_cast<Cx<R>*>(smem));
 }
 
-// Row transform of the split row passes, in place in U.bufA: grid (line blocks, outer, units).
-template <typename R, int RM>
-__global__ __launch_bounds__(kBlock) void k_rows_reg(Geo g, const UnitDev* __restrict__ units, LineArgs a, int inverse) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  Cx<R>* d = reinterpret_cast<Cx<R>*>(units[blockIdx.z].bufA) + blockIdx.y * a.oin;
-  line_body<R, RM>(a, d, d, reinterpret_cast<const Cx<R>*>(g.tw[2]), inverse, reinterpret_cast<Cx<R>*>(smem));
-}
-
 // One array in place (images, GaNi coefficients): grid (line blocks, outer).
 template <typename R, int RM>
 __global__ __launch_bounds__(kBlock) void k_line_reg(Cx<R>* data, LineArgs a, const Cx<R>* __restrict__ tw, int inverse) {
@@ -482,12 +474,11 @@ __global__ __launch_bounds__(kBlock) void k_line_setup(const CoefJob* __restrict
 
 // ============================================================== row passes
 // As the specialised row passes (hom_fast.hip) with run-time lengths: rgG row
-// pairs per block, in 2D one load per block (grid y), in 3D every load.  SPLIT:
-// the lines go through HBM instead of LDS and k_rows_reg transforms them (the
-// same arithmetic per line).
+// pairs per block, in 2D one load per block (grid y), in 3D every load.  Lengths
+// with a split always fit LDS (at most 729 * 11 FP64 values).
 constexpr int kRowPairsMax = 16;
 
-template <typename R, int RM, int D, int DUAL, bool SPLIT>
+template <typename R, int RM, int D, int DUAL>
 __global__ __launch_bounds__(kBlock) void k_first_reg(Geo g, const UnitDev* __restrict__ units, int mode, int jstep,
                                                       const int* __restrict__ iter_base) {
   constexpr int m = DUAL ? D - 1 : 1, LM = D == 2 ? 1 : kMaxLoads, PM = D == 2 ? 1 : kMaxPacks;
@@ -496,7 +487,7 @@ __global__ __launch_bounds__(kBlock) void k_first_reg(Geo g, const UnitDev* __re
   __shared__ int s_act[kMaxLoads];
   __shared__ double s_red[kBlock / 64];
   __shared__ RowInfo s_row[kRowPairsMax];
-  const int M = g.M[2], A = g.rA[2], B = g.rB[2], N2 = g.N[2], N1 = g.N[1], H = (N2 - 1) / 2;
+  const int M = g.M[2], A = g.rA[2], B = g.rB[2], N2 = g.N[2], N1 = g.N[1];
   const int G = g.rgG, L = D == 2 ? 1 : g.L, lo = D == 2 ? (int)blockIdx.y : 0;
   const int P = D == 2 ? 1 : g.P, po = D == 2 ? lo : 0;
   const size_t lstr = g.pmaj ? 1 : (size_t)g.P, pstr = g.pmaj ? (size_t)g.N[0] * N1 * M : 1;
@@ -546,11 +537,9 @@ __global__ __launch_bounds__(kBlock) void k_first_reg(Geo g, const UnitDev* __re
     }
   }
   if (tid < G) row_info(g, blockIdx.x * G + tid, s_row[tid]);
-  if constexpr (!SPLIT) {
-    const Cx<R>* twg = reinterpret_cast<const Cx<R>*>(g.tw[2]);
-    for (int i = tid; i < M; i += kBlock) tw[i] = gload(twg, (size_t)i);
-    for (int i = tid; i < 2 * G * P * M; i += kBlock) stage[i] = rf::mk<R>(0, 0);
-  }
+  const Cx<R>* twg = reinterpret_cast<const Cx<R>*>(g.tw[2]);
+  for (int i = tid; i < M; i += kBlock) tw[i] = gload(twg, (size_t)i);
+  for (int i = tid; i < 2 * G * P * M; i += kBlock) stage[i] = rf::mk<R>(0, 0);
   __syncthreads();
   if (mode == FIRST_CG) {
     int any = 0;
@@ -562,15 +551,6 @@ __global__ __launch_bounds__(kBlock) void k_first_reg(Geo g, const UnitDev* __re
     const int i0 = line ? ri.i0B : ri.h0, i1 = line ? ri.i1B : ri.i1A;
     return (((size_t)i0 * N1 + i1) * M + pos) * lstr + (po + pk) * pstr;
   };
-  if constexpr (SPLIT) {
-    // the zero padding (the entries below write the rest)
-    const int pad = M - N2;
-    for (int t = tid; t < 2 * G * P * pad; t += kBlock) {
-      const int lp = t / pad, pos = H + 1 + (t - lp * pad), ln = lp / P;
-      const RowInfo& ri = s_row[ln >> 1];
-      if (ri.valid && !((ln & 1) && ri.self)) gstore(out, at(ri, ln & 1, pos, lp - ln * P), rf::mk<R>(0, 0));
-    }
-  }
 
   // ---- CG update of the stored entries; packed fields of the rows into the staging area
   double gp[LM];
@@ -632,13 +612,8 @@ __global__ __launch_bounds__(kBlock) void k_first_reg(Geo g, const UnitDev* __re
       }
       const Cx<R> zA = rf::mk<R>((R)(X[0].x - X[1].y), (R)(X[0].y + X[1].x));
       const Cx<R> zB = rf::mk<R>((R)(X[0].x + X[1].y), (R)(-X[0].y + X[1].x));
-      if constexpr (SPLIT) {
-        gstore(out, at(ri, 0, posA, pk), zA);
-        if (!ri.self) gstore(out, at(ri, 1, posB, pk), zB);
-      } else {
-        stage[((size_t)(2 * gi) * P + pk) * M + posA] = zA;
-        if (!ri.self) stage[((size_t)(2 * gi + 1) * P + pk) * M + posB] = zB;
-      }
+      stage[((size_t)(2 * gi) * P + pk) * M + posA] = zA;
+      if (!ri.self) stage[((size_t)(2 * gi + 1) * P + pk) * M + posB] = zB;
     }
   }
   if (mode == FIRST_CG) {
@@ -649,7 +624,6 @@ __global__ __launch_bounds__(kBlock) void k_first_reg(Geo g, const UnitDev* __re
       if (tid == 0) gstore(U.part_g, (size_t)(lo + l) * g.nbF + blockIdx.x, s);
     }
   }
-  if constexpr (SPLIT) return;
   __syncthreads();
 
   // ---- inverse four-step transform of every (line, pack)
@@ -709,7 +683,7 @@ __global__ __launch_bounds__(kBlock) void k_first_reg(Geo g, const UnitDev* __re
   }
 }
 
-template <typename R, int RM, int D, int DUAL, bool SPLIT>
+template <typename R, int RM, int D, int DUAL>
 __global__ __launch_bounds__(kBlock) void k_last_reg(Geo g, const UnitDev* __restrict__ units, int mode, int jstep,
                                                      const int* __restrict__ iter_base) {
   constexpr int m = DUAL ? D - 1 : 1, LM = D == 2 ? 1 : kMaxLoads;
@@ -770,10 +744,8 @@ __global__ __launch_bounds__(kBlock) void k_last_reg(Geo g, const UnitDev* __res
     }
   }
   if (tid < G) row_info(g, blockIdx.x * G + tid, s_row[tid]);
-  if constexpr (!SPLIT) {
-    const Cx<R>* twg = reinterpret_cast<const Cx<R>*>(g.tw[2]);
-    for (int i = tid; i < M; i += kBlock) tw[i] = gload(twg, (size_t)i);
-  }
+  const Cx<R>* twg = reinterpret_cast<const Cx<R>*>(g.tw[2]);
+  for (int i = tid; i < M; i += kBlock) tw[i] = gload(twg, (size_t)i);
   __syncthreads();
   {
     int any = 0;
@@ -786,53 +758,51 @@ __global__ __launch_bounds__(kBlock) void k_last_reg(Geo g, const UnitDev* __res
   };
 
   // ---- forward four-step transform of every (line, pack), natural order in the staging area
-  if constexpr (!SPLIT) {
-    const int nlp = 2 * G * P;
-    with_radix<RM>(B, [&](auto rb) HOM_INL {
-      constexpr int RB = decltype(rb)::value;
-      for (int t = tid; t < nlp * A; t += kBlock) {
-        // 3D: packs fastest (they are interleaved in HBM); 2D has one pack per block
-        int lp, q;
-        if constexpr (D == 3) {
-          const int pk = t % P, r = t / P, ln = r / A;
-          q = r - ln * A;
-          lp = ln * P + pk;
-        } else {
-          lp = t / A;
-          q = t - lp * A;
-        }
-        const int ln = lp / P;
-        const RowInfo& ri = s_row[ln >> 1];
-        if (!ri.valid || ((ln & 1) && ri.self)) continue;
-        const size_t base = at(ri, ln & 1, q, lp - ln * P);
-        Cx<R> v[RB];
-#pragma unroll
-        for (int n2 = 0; n2 < RB; ++n2) v[n2] = gload(in, base + (size_t)(A * n2) * lstr);
-        rf::Dft<R, RB, -1>::run(v);
-        Cx<R>* e = stage + (size_t)lp * M + q * RB;
-#pragma unroll
-        for (int m2 = 0; m2 < RB; ++m2) e[m2] = rf::mul(v[m2], tw[q * m2]);
+  const int nlp = 2 * G * P;
+  with_radix<RM>(B, [&](auto rb) HOM_INL {
+    constexpr int RB = decltype(rb)::value;
+    for (int t = tid; t < nlp * A; t += kBlock) {
+      // 3D: packs fastest (they are interleaved in HBM); 2D has one pack per block
+      int lp, q;
+      if constexpr (D == 3) {
+        const int pk = t % P, r = t / P, ln = r / A;
+        q = r - ln * A;
+        lp = ln * P + pk;
+      } else {
+        lp = t / A;
+        q = t - lp * A;
       }
-    });
-    __syncthreads();
-    with_radix<RM>(A, [&](auto ra) HOM_INL {
-      constexpr int RA = decltype(ra)::value;
-      for (int t = tid; t < nlp * B; t += kBlock) {
-        const int lp = t / B, q = t - lp * B, ln = lp / P;
-        const RowInfo& ri = s_row[ln >> 1];
-        if (!ri.valid || ((ln & 1) && ri.self)) continue;
-        Cx<R>* e = stage + (size_t)lp * M + q;
-        Cx<R> v[RA];
+      const int ln = lp / P;
+      const RowInfo& ri = s_row[ln >> 1];
+      if (!ri.valid || ((ln & 1) && ri.self)) continue;
+      const size_t base = at(ri, ln & 1, q, lp - ln * P);
+      Cx<R> v[RB];
 #pragma unroll
-        for (int n1 = 0; n1 < RA; ++n1) v[n1] = e[B * n1];
-        rf::Dft<R, RA, -1>::run(v);
-        // X[q + B m1] takes the slots this thread read
+      for (int n2 = 0; n2 < RB; ++n2) v[n2] = gload(in, base + (size_t)(A * n2) * lstr);
+      rf::Dft<R, RB, -1>::run(v);
+      Cx<R>* e = stage + (size_t)lp * M + q * RB;
 #pragma unroll
-        for (int m1 = 0; m1 < RA; ++m1) e[B * m1] = v[m1];
-      }
-    });
-    __syncthreads();
-  }
+      for (int m2 = 0; m2 < RB; ++m2) e[m2] = rf::mul(v[m2], tw[q * m2]);
+    }
+  });
+  __syncthreads();
+  with_radix<RM>(A, [&](auto ra) HOM_INL {
+    constexpr int RA = decltype(ra)::value;
+    for (int t = tid; t < nlp * B; t += kBlock) {
+      const int lp = t / B, q = t - lp * B, ln = lp / P;
+      const RowInfo& ri = s_row[ln >> 1];
+      if (!ri.valid || ((ln & 1) && ri.self)) continue;
+      Cx<R>* e = stage + (size_t)lp * M + q;
+      Cx<R> v[RA];
+#pragma unroll
+      for (int n1 = 0; n1 < RA; ++n1) v[n1] = e[B * n1];
+      rf::Dft<R, RA, -1>::run(v);
+      // X[q + B m1] takes the slots this thread read
+#pragma unroll
+      for (int m1 = 0; m1 < RA; ++m1) e[B * m1] = v[m1];
+    }
+  });
+  __syncthreads();
 
   // ---- epilogue: unpack, project (T^T), CG direction update, <r, C r>
   double dp[LM];
@@ -853,8 +823,7 @@ __global__ __launch_bounds__(kBlock) void k_last_reg(Geo g, const UnitDev* __res
     double Tb[3][2];
     basis_t<D, DUAL>(g, kk0, kk1, k2, Tb);
     auto z_at = [&](int line, int pos, int pk) -> Cx<R> {
-      if constexpr (SPLIT) return gload(in, at(re, line, pos, pk));
-      else return stage[((size_t)(2 * gi + line) * P + pk) * M + pos];
+      return stage[((size_t)(2 * gi + line) * P + pk) * M + pos];
     };
 #pragma unroll
     for (int l = 0; l < LM; ++l) {
@@ -970,73 +939,31 @@ static size_t row_lds(const Geo& g) {
 }
 
 template <typename R, int RM, int D, int DUAL>
-static hipError_t run_row_reg(bool first, bool split, const Geo& g, const UnitDev* units, int n, int mode, int jstep,
-                              const int* ib, hipStream_t st) {
+static hipError_t run_row_reg(bool first, const Geo& g, const UnitDev* units, int n, int mode, int jstep, const int* ib,
+                              hipStream_t st) {
   const dim3 grid((g.Q + g.rgG - 1) / g.rgG, D == 2 ? g.L : 1, n);
-  if (split) {
-    // radix-free gather and epilogue: one instance (class 9) serves every length
-    if (first) return launch_line(k_first_reg<R, 9, D, DUAL, true>, grid, 0, st, g, units, mode, jstep, ib);
-    return launch_line(k_last_reg<R, 9, D, DUAL, true>, grid, 0, st, g, units, mode, jstep, ib);
-  }
-  if (first) return launch_line(k_first_reg<R, RM, D, DUAL, false>, grid, row_lds<R>(g), st, g, units, mode, jstep, ib);
-  return launch_line(k_last_reg<R, RM, D, DUAL, false>, grid, row_lds<R>(g), st, g, units, mode, jstep, ib);
+  if (first) return launch_line(k_first_reg<R, RM, D, DUAL>, grid, row_lds<R>(g), st, g, units, mode, jstep, ib);
+  return launch_line(k_last_reg<R, RM, D, DUAL>, grid, row_lds<R>(g), st, g, units, mode, jstep, ib);
 }
 
 template <typename R, int D, int DUAL>
-static hipError_t run_row_class(bool first, bool split, const Geo& g, const UnitDev* units, int n, int mode, int jstep,
-                                const int* ib, hipStream_t st) {
-#define HOM_C(RM) run_row_reg<R, RM, D, DUAL>(first, split, g, units, n, mode, jstep, ib, st)
+static hipError_t run_row_class(bool first, const Geo& g, const UnitDev* units, int n, int mode, int jstep, const int* ib,
+                                hipStream_t st) {
+#define HOM_C(RM) run_row_reg<R, RM, D, DUAL>(first, g, units, n, mode, jstep, ib, st)
   HOM_RCLASS(g.rA[2], g.rB[2], HOM_C);
 #undef HOM_C
 }
 
 template <typename R>
-static hipError_t run_rows_split(const Geo& g, const UnitDev* units, int n, int inverse, hipStream_t st) {
-  LineArgs a{};
-  a.A = g.rA[2];
-  a.B = g.rB[2];
-  a.M = a.N = g.M[2];
-  const int T = a.A > a.B ? a.A : a.B;
-  int outer;
-  if (g.pmaj || g.P == 1) {  // rows contiguous
-    a.lines = g.P * g.N[0] * g.N[1];
-    a.rowwise = 1;
-    a.stride = 1;
-    a.lstep = a.M;
-    outer = 1;
-  } else {
-    a.lines = g.P;
-    a.stride = g.P;
-    a.lstep = 1;
-    a.oin = a.oout = (size_t)a.M * g.P;
-    outer = g.N[0] * g.N[1];
-    if (outer > 65535) return hipErrorInvalidValue;
-  }
-  a.nl = kBlock / T;
-  while (a.nl > 1 && (size_t)a.M * a.nl * sizeof(Cx<R>) > 64 * 1024) --a.nl;
-  if (a.nl > a.lines) a.nl = a.lines;
-  const dim3 grid((a.lines + a.nl - 1) / a.nl, outer, n);
-  const size_t lds = (size_t)a.M * a.nl * sizeof(Cx<R>);
-#define HOM_C(RM) launch_line(k_rows_reg<R, RM>, grid, lds, st, g, units, a, inverse)
-  HOM_RCLASS(a.A, a.B, HOM_C);
-#undef HOM_C
-}
-
-template <typename R>
-bool reg_row(bool first, bool split, const Geo& g, const UnitDev* units, int n, int mode, int jstep, const int* ib,
-             hipStream_t st, hipError_t* err) {
+bool reg_row(bool first, const Geo& g, const UnitDev* units, int n, int mode, int jstep, const int* ib, hipStream_t st,
+             hipError_t* err) {
   if (!g.rA[2]) return false;
-  if (split && !first) {
-    *err = run_rows_split<R>(g, units, n, 0, st);
-    if (*err != hipSuccess) return true;
-  }
   if (g.d == 2)
-    *err = g.dual ? run_row_class<R, 2, 1>(first, split, g, units, n, mode, jstep, ib, st)
-                  : run_row_class<R, 2, 0>(first, split, g, units, n, mode, jstep, ib, st);
+    *err = g.dual ? run_row_class<R, 2, 1>(first, g, units, n, mode, jstep, ib, st)
+                  : run_row_class<R, 2, 0>(first, g, units, n, mode, jstep, ib, st);
   else
-    *err = g.dual ? run_row_class<R, 3, 1>(first, split, g, units, n, mode, jstep, ib, st)
-                  : run_row_class<R, 3, 0>(first, split, g, units, n, mode, jstep, ib, st);
-  if (split && first && *err == hipSuccess) *err = run_rows_split<R>(g, units, n, 1, st);
+    *err = g.dual ? run_row_class<R, 3, 1>(first, g, units, n, mode, jstep, ib, st)
+                  : run_row_class<R, 3, 0>(first, g, units, n, mode, jstep, ib, st);
   return true;
 }
 

@@ -4,7 +4,7 @@
 namespace hom {
 namespace ln {
 
-template bool reg_row<float>(bool, bool, const Geo&, const UnitDev*, int, int, int, const int*, hipStream_t, hipError_t*);
+template bool reg_row<float>(bool, const Geo&, const UnitDev*, int, int, int, const int*, hipStream_t, hipError_t*);
 template bool reg_mid<float>(const Geo&, const UnitDev*, int, int, hipStream_t, hipError_t*);
 template bool reg_col<float>(const Geo&, const UnitDev*, int, int, hipStream_t, hipError_t*);
 

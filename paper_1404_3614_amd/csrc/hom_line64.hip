@@ -4,7 +4,7 @@
 namespace hom {
 namespace ln {
 
-template bool reg_row<double>(bool, bool, const Geo&, const UnitDev*, int, int, int, const int*, hipStream_t, hipError_t*);
+template bool reg_row<double>(bool, const Geo&, const UnitDev*, int, int, int, const int*, hipStream_t, hipError_t*);
 template bool reg_mid<double>(const Geo&, const UnitDev*, int, int, hipStream_t, hipError_t*);
 template bool reg_col<double>(const Geo&, const UnitDev*, int, int, hipStream_t, hipError_t*);
 template bool reg_line<double>(Cx<double>*, int, int, int, const Cx<double>*, int, hipStream_t, hipError_t*);
