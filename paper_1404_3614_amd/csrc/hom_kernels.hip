@@ -1227,8 +1227,8 @@ static int max_butterflies(const Plan& pl, int M, int nl) {
 
 // M = A B with both factors in the radix set of the register passes, the
 // larger as small as possible (fewer registers, more threads per line); false
-// when there is no such split (lengths above 729, 512, 640) or the generic
-// passes are asked for.
+// when there is no such split (512, 640, 720 and lengths above 729) or the
+// generic passes are asked for.
 bool reg_split(int M, int* A, int* B) {
   static const int kRadix[] = {1, 2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27};
   *A = *B = 0;

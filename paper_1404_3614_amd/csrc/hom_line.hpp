@@ -1,6 +1,6 @@
 // Passes with register four-step transforms of any length M = A * B whose
 // factors are in the radix set below (every 2/3/5-smooth length up to 729 but
-// a few powers of two), in FP32 or FP64 and for any N <= M: the lengths and
+// 512, 640 and 720), in FP32 or FP64 and for any N <= M: the lengths and
 // types that have no compile-time specialisation.
 //
 // What bounds them is memory traffic and latency, so a line makes one LDS

@@ -71,3 +71,44 @@ def test_quadrature_route(N, M, same, full, dual, monkeypatch):
     x = _fields(pb, dual)
     a, b = _both(monkeypatch, lambda: pb.bounds(None, x)["B_up"] if dual else pb.bounds(x, None)["A_up"])
     _check(a, b, same)
+
+
+# every class of split takes the register passes; 512, 640, 720 and lengths above 729 have none
+@pytest.mark.parametrize("M,grid,same", [
+    ((45, 45), None, False), ((81, 1125), None, False), ((1125, 243), None, False), ((225, 135), None, False),
+    ((405, 375), None, False), ((729, 625), None, False), ((1125, 1125), None, True),
+    ((1125, 1125), (512, 512), True), ((1875, 1875), (640, 640), True), ((1875, 1875), (720, 720), True),
+    ((1215, 1215), (600, 500), False), ((1215, 1215), (576, 480), False)])
+def test_lengths_with_a_split(M, grid, same, monkeypatch):
+    N = tuple(g - 1 for g in grid) if grid else tuple((m + 1) // 4 * 2 - 1 for m in M)
+    pb = _problem(N, M, False)
+    if grid:
+        cell = homgen.square_inclusion_cell(2, side=0.5, rho_in=12.0, Y=np.array(pb.Y))
+        pb.set_gani_from_cell(cell, grid=grid)
+    for dual in (False, True):
+        x = _fields(pb, dual)[0]
+        a, b = _both(monkeypatch, lambda: pb.apply(x, dual).cpu().numpy())
+        _check(a, b, same)
+
+
+# mixed mode: a specialised pass on one 2D axis and register passes on the other share a pack-major buffer.
+# FP32 operator 2e-6 and bounds of whole solves 1e-6, as for two specialised passes
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("N,M", [((13, 23), (25, 45)), ((41, 121), (81, 243)), ((63, 113), (125, 225)),
+                                 ((23, 13), (45, 25)), ((121, 41), (243, 81)), ((113, 63), (225, 125))])
+def test_mixed_routes(N, M, full, monkeypatch):
+    import paper_1404_3614_amd as H
+    cell = homgen.Inclusions(d=2, Y=np.array([1.0, 1.3]), A0=np.eye(2))
+    cell.add("rect", [0.2, -0.1], [0.3, 0.5], np.diag([4.0, 9.0]) if full else 12.0 * np.eye(2))
+    pb = H.problem_from_cell(cell, N, precision="mixed", M=M)
+    for dual in (False, True):
+        x = _fields(pb, dual)[0]
+        a, b = _both(monkeypatch, lambda: pb.apply(x, dual).cpu().numpy())
+        assert np.abs(a - b).max() <= 2e-6 * np.abs(b).max() and not np.array_equal(a, b)
+    exact = H.problem_from_cell(cell, N, precision="fp64", M=M)
+    monkeypatch.setenv("HOM_NO_FAST", "1")
+    ref = exact.solve_bounds(tol=1e-8)
+    monkeypatch.delenv("HOM_NO_FAST")
+    got = pb.solve_bounds(tol=1e-8)
+    for k in ("A_up", "A_low"):
+        assert np.abs(got[k] - ref[k]).max() <= 1e-6 * np.abs(ref[k]).max()
