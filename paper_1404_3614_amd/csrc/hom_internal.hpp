@@ -13,7 +13,7 @@ namespace hom {
 constexpr int kMaxLoads = 3;      // loads solved together per coefficient field
 constexpr int kMaxPacks = 5;      // ceil(3 loads * 3 components / 2)
 constexpr size_t kLdsMax = 160 * 1024;  // LDS bytes per workgroup (gfx950)
-constexpr int kMaxStages = 12;    // radix-3/5 stages per FFT length
+constexpr int kMaxStages = 9;     // radix stages per FFT length: 3^8 is the most that a line in LDS (10240 FP64 values) holds
 constexpr int kBlock = 256;       // threads per block of every pipeline kernel
 
 template <typename R>
@@ -94,7 +94,9 @@ struct UnitDev {
   const float* coefp;                // FP32 coefficient in plane order [M2][nc][M0][M1] (plane pass), or null
 };
 
-// Shape information shared by every unit of a launch (passed by value).
+// Shape information shared by every unit of a launch (passed by value: its
+// 64-byte lines are read at each launch, and 40 bytes more, a seventh line, cost
+// the specialised row passes 0.2 of 4.2 us per launch on small grids).
 struct Geo {
   int d;               // physical dimension
   int N[3], M[3];      // internal sizes (N[1] = M[1] = 1 for d = 2)
@@ -114,7 +116,7 @@ struct Geo {
   int apTP;            // points per block of the specialised column pass (0: default)
   int apHX;            // 2D column pass: exchange real and imaginary parts separately
   int apAll;           // 2D column pass: all packs of a point block in one block
-  int pmaj;            // 2D, both specialised passes: row-pass buffer pack-major [P][N0][M2]
+  int pmaj;            // 2D, register transforms on both axes: row-pass buffer pack-major [P][N0][M2]
                        // (otherwise [N0][N1][M2][P], packs interleaved)
   int plane;           // 3D: the coefficient product runs as one plane pass (fast_plane), no middle passes
   // register passes of any length (hom_line.hpp): factors of M_a (0: none), row pairs per row-pass
@@ -127,6 +129,7 @@ struct Geo {
   Plan pl[3];
   const void* tw[3];   // R-typed twiddles exp(-2 pi i t / M_a), t < M_a
 };
+static_assert(sizeof(Geo) <= 336, "with the row passes' other arguments within six lines");
 
 // *_PROF: the memory traffic of a CG iteration with zero step lengths and no
 // scalar updates, on scratch vectors (tile tuning of the specialised passes).
